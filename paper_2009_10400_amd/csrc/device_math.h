@@ -214,20 +214,17 @@ __device__ __forceinline__ void element_physics(const KMat &m, const float H[9],
             for (int i = 0; i < 3; ++i) o.qV[i] = Ad[3 * i] * z[0] + Ad[3 * i + 1] * z[1] + Ad[3 * i + 2] * z[2];
         }
     }
-    // ---- thermal split, Eqs. 7-8, 11.  A: the gradient the strain is formed from, F_e - I, or H = F - I when
-    // the expansion is isotropic (F_e = F / l_i)
+    // ---- thermal split, Eqs. 7-8, 11: A = F_e - I
     const float li1 = stretch_m1(m, m.alpha, dTe);
     const float li = 1.0f + li1, inv_li = rcp(li);
     float A[9];
 #pragma unroll
-    for (int i = 0; i < 9; ++i) A[i] = H[i];
+    for (int i = 0; i < 9; ++i) A[i] = H[i] * inv_li;
+    A[0] -= li1 * inv_li;
+    A[4] -= li1 * inv_li;
+    A[8] -= li1 * inv_li;
     float beta = 0.0f, lm = 1.0f;
     if (expan_mode != 0) {
-#pragma unroll
-        for (int i = 0; i < 9; ++i) A[i] = H[i] * inv_li;
-        A[0] -= li1 * inv_li;
-        A[4] -= li1 * inv_li;
-        A[8] -= li1 * inv_li;
         // F_e = F/li + b_m (F m) (x) m [+ b_n (F n) (x) n], b = 1/l - 1/li = (li1 - l1)/(li l)
         const float lm1 = stretch_m1(m, m.alpha_m, dTe);
         lm = 1.0f + lm1;
@@ -241,46 +238,38 @@ __device__ __forceinline__ void element_physics(const KMat &m, const float H[9],
             add_axis_term(A, H, nv, (li1 - ln1) * inv_li * rcp(1.0f + ln1));
         }
     }
-    // ---- elastic strain and stress S_i (Eq. 9).  Isotropic expansion keeps the total G and N and scales what
-    // enters the stress: G_e = (G - (l_i^2 - 1) I) / l_i^2, N_e = l_i^2 N - (l_i^2 - 1) I
+    // ---- elastic strain and stress S_i (Eq. 9)
     const Sym3 G = strain2(A);
-    const float JA1 = det_m1(A);
-    float trG = G.xx + G.yy + G.zz;
-    const Sym3 N = one_minus_inverse(G, JA1, trG);
-    if (iso) {
-        Jt = 1.0f + JA1;
-        inverse_apply(N, gT, V0 * m.k * kscale * Jt, o.qV);
+    const float Jm1 = det_m1(A);
+    const float J = 1.0f + Jm1;
+    const float trG = G.xx + G.yy + G.zz;
+    const Sym3 N = one_minus_inverse(G, Jm1, trG);
+    if (iso) {   // F = l_i F_e: J F^-1 F^-T = l_i J_e C_e^-1
+        const float Jl = J * li;
+        Jt = Jl * (li * li);
+        inverse_apply(N, gT, V0 * m.k * kscale * Jl, o.qV);
     }
     const Sym3 aa{a[0] * a[0], a[1] * a[1], a[2] * a[2], a[0] * a[1], a[1] * a[2], a[0] * a[2]};
     float scale = 1.0f;
     if (m.muT_on) scale = 1.0f - m.muT_drop * clamp01f((dTe + m.muT_off) * m.muT_inv);
     const float mu = m.mu * scale, eta = m.eta * scale;
-    float aGa = 2.0f * (G.xy * aa.xy + G.yz * aa.yz + G.xz * aa.xz) + G.xx * aa.xx + G.yy * aa.yy + G.zz * aa.zz;
-    float Jm1 = JA1;
-    const float l2 = li1 * (2.0f + li1);          // l_i^2 - 1
-    if (expan_mode == 0) {
-        const float s2 = inv_li * inv_li;
-        trG = s2 * (trG - 3.0f * l2);
-        aGa = s2 * (aGa - l2);
-        Jm1 = (JA1 - (l2 + li1 + l2 * li1)) * (s2 * inv_li);
-    }
-    const float J = 1.0f + Jm1;
+    const float aGa = 2.0f * (G.xy * aa.xy + G.yz * aa.yz + G.xz * aa.xz) + G.xx * aa.xx + G.yy * aa.yy + G.zz * aa.zz;
     const float j23m1 = pow_m23_m1(Jm1);
     const float j23 = 1.0f + j23m1;
     const float I4 = 1.0f + aGa;
     const float I4b1 = j23m1 + j23 * aGa;  // I4bar - 1
     const float ciso = mu * j23;
     const float cvol = m.kappa * J * Jm1;
-    // S_i = cN N_e + cI I + cA a (x) a: mu J^-2/3 (I - I1/3 C^-1), the fibre term and kappa J (J - 1) C^-1;
-    // with isotropic expansion N_e and the pull-back det(Fth) / l_i^2 = l_i (Eq. 10) go into the scalars
+    // S_i = cN N + cI I + cA a (x) a: mu J^-2/3 (I - I1/3 C^-1), the fibre term and kappa J (J - 1) C^-1;
+    // with isotropic expansion the pull-back det(Fth) / l_i^2 = l_i (Eq. 10) goes into the scalars
     float cA = 2.0f * eta * I4b1 * j23;
     const float cfc = cvol - cA * I4 * (1.0f / 3.0f);
     const float t3 = trG * (1.0f / 3.0f);
     float cN = ciso * (1.0f + t3) - cfc, cI = cfc - ciso * t3;
     if (expan_mode == 0) {
         cA *= li;
-        cI = li * (cI - cN * l2);
-        cN *= li * (1.0f + l2);
+        cI *= li;
+        cN *= li;
     }
     Sym3 S;
     S.xx = cA * aa.xx + (cN * N.xx + cI);
