@@ -1318,7 +1318,6 @@ struct tled_mlp {
     std::mutex in_call;
     hipStream_t kept_stream = nullptr;
     hipEvent_t done = nullptr;
-    hipStream_t done_stream = nullptr;
     bool done_valid = false;
     // timing
     bool timing = false;
@@ -1849,10 +1848,12 @@ void tled_mlp_destroy(tled_mlp *s) {
     delete s;
 }
 
-// Work on stream from here on comes after what calls on other streams have enqueued.  A
+// Work on stream from here on comes after what earlier calls have enqueued, whatever their
+// streams: a handle's value does not tell one stream from another (hipStreamPerThread is
+// one value for a stream per thread, and a destroyed stream's address is used again).  A
 // stream under capture is left alone: an event from outside must not enter its graph.
 static tled_status order_after_calls(tled_mlp *s, hipStream_t stream) {
-    if (!s->done_valid || stream == s->done_stream) return TLED_OK;
+    if (!s->done_valid) return TLED_OK;
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     MCHK(s, hipStreamIsCapturing(stream, &capture));
     if (capture == hipStreamCaptureStatusNone) MCHK(s, hipStreamWaitEvent(stream, s->done, 0));
@@ -1883,7 +1884,6 @@ tled_status tled_mlp_end(tled_mlp *s) {
     if (e == hipSuccess && capture == hipStreamCaptureStatusNone) {
         e = hipEventRecord(s->done, stream);
         s->done_valid = s->done_valid || e == hipSuccess;
-        s->done_stream = stream;
     }
     s->stream = s->kept_stream;
     const tled_status st = e == hipSuccess ? TLED_OK : mfail(s, TLED_E_HIP, hipGetErrorString(e));
