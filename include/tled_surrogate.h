@@ -63,7 +63,8 @@ tled_status tled_mlp_set_stream(tled_mlp *mlp, void *hip_stream);
  * the null stream) instead of its own: after the caller's earlier work there, with no
  * events between two streams, and after calls begun on other streams.  Another
  * thread's begin, get_params, set_params and set_stream wait for the end.  Every
- * begin that returned TLED_OK needs its end.  A handle is used either this way or
+ * begin that returned TLED_OK needs its end; a second begin, a set_stream in
+ * between, or an end by a thread that has not begun returns TLED_E_STATE.  A handle is used either this way or
  * directly on its own stream.  Under stream capture the calls become part of the
  * graph; nothing orders its replays after calls on other streams. */
 tled_status tled_mlp_begin(tled_mlp *mlp, void *hip_stream);

@@ -4,11 +4,13 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstring>
 #include <mutex>
 #include <new>
 #include <string>
+#include <thread>
 #include <type_traits>
 #include <utility>
 #include <vector>
@@ -1313,9 +1315,10 @@ struct tled_mlp {
     std::string err;
     float *d_split = nullptr;        // split-K partials
     size_t split_cap = 0;
-    // calls on their caller's stream (tled_mlp_begin): the handle's own stream meanwhile, and
-    // what the last of them left behind
+    // calls on their caller's stream (tled_mlp_begin): the thread between begin and end, the
+    // handle's own stream meanwhile, and what the last of them left behind
     std::mutex in_call;
+    std::atomic<std::thread::id> caller{};
     hipStream_t kept_stream = nullptr;
     hipEvent_t done = nullptr;
     bool done_valid = false;
@@ -1860,8 +1863,17 @@ static tled_status order_after_calls(tled_mlp *s, hipStream_t stream) {
     return TLED_OK;
 }
 
+// Whether this thread is between begin and end (it then holds in_call).
+static bool in_own_call(const tled_mlp *s) { return s->caller.load() == std::this_thread::get_id(); }
+
+// Holds in_call over a call that may also be made between begin and end.
+static std::unique_lock<std::mutex> call_lock(tled_mlp *s) {
+    return in_own_call(s) ? std::unique_lock<std::mutex>() : std::unique_lock<std::mutex>(s->in_call);
+}
+
 tled_status tled_mlp_begin(tled_mlp *s, void *hip_stream) {
     if (!s) return TLED_E_ARG;
+    if (in_own_call(s)) return mfail(s, TLED_E_STATE, "begin without the end of the one before");
     s->in_call.lock();
     const hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     tled_status st = TLED_OK;
@@ -1873,11 +1885,13 @@ tled_status tled_mlp_begin(tled_mlp *s, void *hip_stream) {
     }
     s->kept_stream = s->stream;
     s->stream = stream;
+    s->caller = std::this_thread::get_id();
     return TLED_OK;
 }
 
 tled_status tled_mlp_end(tled_mlp *s) {
     if (!s) return TLED_E_ARG;
+    if (!in_own_call(s)) return TLED_E_STATE;     // nothing is written: another thread may be in its calls
     const hipStream_t stream = s->stream;
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     hipError_t e = hipStreamIsCapturing(stream, &capture);
@@ -1886,6 +1900,7 @@ tled_status tled_mlp_end(tled_mlp *s) {
         s->done_valid = s->done_valid || e == hipSuccess;
     }
     s->stream = s->kept_stream;
+    s->caller = std::thread::id();
     const tled_status st = e == hipSuccess ? TLED_OK : mfail(s, TLED_E_HIP, hipGetErrorString(e));
     s->in_call.unlock();
     return st;
@@ -1893,6 +1908,7 @@ tled_status tled_mlp_end(tled_mlp *s) {
 
 tled_status tled_mlp_set_stream(tled_mlp *s, void *hip_stream) {
     if (!s) return TLED_E_ARG;
+    if (in_own_call(s)) return mfail(s, TLED_E_STATE, "set_stream between begin and end");
     std::lock_guard<std::mutex> lock(s->in_call);
     MCHK(s, hipStreamSynchronize(s->stream));
     if (s->done_valid) MCHK(s, hipEventSynchronize(s->done));
@@ -1914,7 +1930,7 @@ tled_status tled_mlp_param_count(const tled_mlp *s, int64_t *n) {
 
 tled_status tled_mlp_get_params(tled_mlp *s, float *host) {
     if (!s || !host) return TLED_E_ARG;
-    std::lock_guard<std::mutex> lock(s->in_call);
+    const std::unique_lock<std::mutex> lock = call_lock(s);
     MCHK(s, hipSetDevice(s->device));
     MTRY(order_after_calls(s, s->stream));
     MCHK(s, hipMemcpyAsync(host, s->d_w, sizeof(float) * s->P, hipMemcpyDeviceToHost, s->stream));
@@ -1924,7 +1940,7 @@ tled_status tled_mlp_get_params(tled_mlp *s, float *host) {
 
 tled_status tled_mlp_set_params(tled_mlp *s, const float *host) {
     if (!s || !host) return TLED_E_ARG;
-    std::lock_guard<std::mutex> lock(s->in_call);
+    const std::unique_lock<std::mutex> lock = call_lock(s);
     MCHK(s, hipSetDevice(s->device));
     MTRY(order_after_calls(s, s->stream));
     MCHK(s, hipMemcpyAsync(s->d_w, host, sizeof(float) * s->P, hipMemcpyHostToDevice, s->stream));
