@@ -492,6 +492,7 @@ class Ensemble:
         # coordinates and tables in one upload, 8-byte items first (joining the coordinates and
         # a copy for each table took 0.1 ms more for 16 scenarios)
         parts = [("X", np.ascontiguousarray(p.X, np.float64)) for p, _ in items]
+        np.concatenate([a[:0] for _, a in parts])      # refuses no items, and coordinates that do not join
         parts += [("offs", offs), ("probe", probe), ("xi", xi), ("prm", prm), ("T0", T0), ("sT", sT), ("su", su)]
         host = np.concatenate([a.reshape(-1).view(np.uint8) for _, a in parts])
         packed = torch.from_numpy(host).to(dev)
