@@ -203,6 +203,16 @@ void *dev_alloc(tled_sim *s, size_t bytes) {
     return p;
 }
 
+// Gives back the device buffers from number `keep` on.
+void release_bufs(tled_sim *s, size_t keep) {
+    for (size_t i = keep; i < s->bufs.size(); ++i) {
+        if (s->release) s->release(s->bufs[i].p, s->actx);
+        else (void)hipFree(s->bufs[i].p);
+        s->device_bytes -= int64_t(s->bufs[i].bytes);
+    }
+    s->bufs.resize(keep);
+}
+
 tled_status resident_register(tled_sim *s) {
     HIPCHK(s, hipEventCreateWithFlags(&s->res_ev, hipEventDisableTiming));
     std::lock_guard<std::mutex> lock(g_resident_mu);
@@ -257,12 +267,7 @@ void free_device(tled_sim *s) {
     resident_unregister(s);
     s->resident = false;
     drop_graphs(s);
-    for (auto &b : s->bufs) {
-        if (s->release) s->release(b.p, s->actx);
-        else (void)hipFree(b.p);
-    }
-    s->bufs.clear();
-    s->device_bytes = 0;
+    release_bufs(s, 0);
 }
 
 template <typename T>
@@ -407,15 +412,23 @@ tled_status setup_resident(tled_sim *s) {
         sr[2 * q] = P.srow[sn];
         sr[2 * q + 1] = P.srow[sn + 1];
     }
-    int *dsr;
-    TRY(upload(s, &dsr, sr));
-    r.srange = reinterpret_cast<const int2 *>(dsr);
-    TRY(zeros(s, &r.xbuf, size_t(3) * r.n_entries));
-    TRY(zeros(s, &r.sync, kResidentSyncWords));
-    if (s->dose_on) {
-        s->hist_steps = s->opt.graph_steps > 0 ? std::min(s->opt.graph_steps, 100) : 100;
-        TRY(zeros(s, &r.hist, size_t(s->hist_steps) * r.nn));
+    // the per-step launches need none of this memory: without it they run
+    const size_t held = s->bufs.size();
+    const int hist_steps = s->opt.graph_steps > 0 ? std::min(s->opt.graph_steps, 100) : 100;
+    int *dsr = static_cast<int *>(dev_alloc(s, sizeof(int32_t) * sr.size()));
+    r.xbuf = dsr ? static_cast<float4 *>(dev_alloc(s, sizeof(float4) * 3 * size_t(r.n_entries))) : nullptr;
+    r.sync = r.xbuf ? static_cast<unsigned *>(dev_alloc(s, sizeof(unsigned) * kResidentSyncWords)) : nullptr;
+    if (r.sync && s->dose_on) r.hist = static_cast<float *>(dev_alloc(s, sizeof(float) * hist_steps * size_t(r.nn)));
+    if (!r.sync || (s->dose_on && !r.hist)) {
+        release_bufs(s, held);
+        (void)hipGetLastError();                  // a failed hipMalloc's, or the next launch would report it
+        r = ResidentArgs{};
+        return TLED_OK;
     }
+    if (r.hist) s->hist_steps = hist_steps;
+    r.srange = reinterpret_cast<const int2 *>(dsr);
+    HIPCHK(s, hipMemcpyAsync(dsr, sr.data(), sizeof(int32_t) * sr.size(), hipMemcpyHostToDevice, s->stream));
+    HIPCHK(s, hipMemsetAsync(r.sync, 0, sizeof(unsigned) * kResidentSyncWords, s->stream));
     HIPCHK(s, hipStreamSynchronize(s->stream));   // sr is uploaded asynchronously
     TRY(resident_register(s));
     s->resident = true;
