@@ -254,6 +254,13 @@ tled_status tled_finalize(tled_sim *sim);
  * stream, in hipGraph chunks (tled_options.graph_steps).  Monitors are
  * reduced at the last step of every chunk. */
 tled_status tled_step(tled_sim *sim, int64_t n_steps);
+/* Small and medium problems (every patch of the mesh resident on the GPU at once, the
+ * default kernels and shared_update 0) run chunks of four or more steps in one kernel.
+ * chunks: those enqueued since tled_finalize; given_up: those among them whose workgroups
+ * did not all come to run in time because others held the GPU, so that their steps were
+ * done in another way (with the same results).  Either pointer may be NULL.  Waits for
+ * the stream. */
+tled_status tled_resident_counts(tled_sim *sim, int64_t *chunks, int64_t *given_up);
 /* Captures and instantiates, without running anything, the hipGraphs that a
  * following tled_step(sim, n_steps) replays: the chunk of graph_steps steps and
  * a shorter last chunk.  A last chunk shorter than graph_steps is otherwise

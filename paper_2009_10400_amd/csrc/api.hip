@@ -66,6 +66,7 @@ struct tled_sim {
         int k, np;
         int64_t ns;
         uint64_t used;
+        bool resident;
     };
     std::vector<GraphEntry> graphs;
     uint64_t graph_clock = 0;
@@ -104,6 +105,7 @@ struct tled_sim {
     int res_cap = 0, hist_steps = 0;
     ResidentArgs ra{};
     hipEvent_t res_ev = nullptr;
+    int64_t res_chunks = 0;            // run in the resident kernel since finalize
     // thermal dose (tled_set_thermal_dose): per node (CEM43 minutes, Arrhenius integral)
     bool dose_on = false;
     double dose_A = 0.0, dose_Ea = 0.0;
@@ -762,6 +764,7 @@ tled_status enqueue_chunk(tled_sim *s, int k, int64_t step0, bool captured,
         if (resident_chunk(s, k, pa.n_patches)) {
             launch_resident(npe, s->np, pa, s->ra, k, s->d_step, s->d_mon, s->d_dose, s->dq, s->stream);
             HIPCHK(s, hipGetLastError());
+            if (!captured) ++s->res_chunks;
             return TLED_OK;
         }
     }
@@ -872,10 +875,18 @@ tled_status build_graph(tled_sim *s, int k, int64_t step0, hipGraphExec_t *out) 
         (void)hipGraphExecDestroy(lru->exec);
         s->graphs.erase(lru);
     }
-    tled_sim::GraphEntry ge{exec, k, 0, 0, ++s->graph_clock};
+    tled_sim::GraphEntry ge{exec, k, 0, 0, ++s->graph_clock, false};
     active_counts(s, step0, &ge.np, &ge.ns);
+    ge.resident = resident_chunk(s, k, ge.np);
     s->graphs.push_back(ge);
     *out = exec;
+    return TLED_OK;
+}
+
+tled_status launch_graph(tled_sim *s, hipGraphExec_t g) {
+    HIPCHK(s, hipGraphLaunch(g, s->stream));
+    for (const auto &e : s->graphs)
+        if (e.exec == g && e.resident) ++s->res_chunks;
     return TLED_OK;
 }
 
@@ -1227,6 +1238,16 @@ tled_status tled_finalize(tled_sim *sim) {
     return TLED_OK;
 }
 
+tled_status tled_resident_counts(tled_sim *sim, int64_t *chunks, int64_t *given_up) {
+    TRY(need_device(sim));
+    unsigned st[2] = {0, 0};
+    HIPCHK(sim, hipMemcpyAsync(st, sim->d_status, sizeof(st), hipMemcpyDeviceToHost, sim->stream));
+    HIPCHK(sim, hipStreamSynchronize(sim->stream));
+    if (chunks) *chunks = sim->res_chunks;
+    if (given_up) *given_up = st[1];
+    return TLED_OK;
+}
+
 tled_status tled_step(tled_sim *sim, int64_t n_steps) {
     TRY(need_device(sim));
     if (n_steps < 0) return fail(sim, TLED_E_ARG, "negative step count");
@@ -1249,7 +1270,7 @@ tled_status tled_step(tled_sim *sim, int64_t n_steps) {
             // first step: captured again when that prefix has changed
             hipGraphExec_t g;
             TRY(get_graph(sim, k, cur, &g));
-            HIPCHK(sim, hipGraphLaunch(g, sim->stream));
+            TRY(launch_graph(sim, g));
             left -= k;
             cur += k;
         }
@@ -1257,7 +1278,7 @@ tled_status tled_step(tled_sim *sim, int64_t n_steps) {
         // (tled_prepare_steps captures it), else it is enqueued eagerly
         if (left > 0) {
             if (hipGraphExec_t g = find_graph(sim, int(left), cur)) {
-                HIPCHK(sim, hipGraphLaunch(g, sim->stream));
+                TRY(launch_graph(sim, g));
                 cur += left;
                 left = 0;
             }

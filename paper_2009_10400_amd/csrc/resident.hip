@@ -78,15 +78,16 @@ __device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)
 
 // Arrival at the meeting, thread 0: workgroup b of G counts itself in its group's word
 // (kMeetGroups words on lines of their own, since arrivals at one address are served one
-// after the other); each group's last counts the group, and the last group decides.
-__device__ __forceinline__ void arrive(unsigned *sync, unsigned b, unsigned G) {
+// after the other); each group's last counts the group, and the last group decides (with
+// no patience at all: to give up).
+__device__ __forceinline__ void arrive(unsigned *sync, unsigned b, unsigned G, long long ticks) {
     const unsigned g = b % kMeetGroups, groups = min(G, unsigned(kMeetGroups));
     const unsigned size = G / kMeetGroups + (g < G % kMeetGroups ? 1 : 0);
     if (__hip_atomic_fetch_add(&sync[kMeetStride * (2 + g)], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 < size)
         return;
     if (__hip_atomic_fetch_add(&sync[kMeetStride], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 < groups) return;
     unsigned undecided = 0;
-    __hip_atomic_compare_exchange_strong(&sync[0], &undecided, kGo, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+    __hip_atomic_compare_exchange_strong(&sync[0], &undecided, ticks > 0 ? kGo : kAbort, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
                                          __HIP_MEMORY_SCOPE_AGENT);
 }
 
@@ -187,7 +188,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(NPE == 8
             for (int b = 0; b < 3; ++b) x.put(u32x4{kEmpty, kEmpty, kEmpty, kEmpty}, b, A.ppos[q]);
         stores_done();
         __syncthreads();
-        if (threadIdx.x == 0) arrive(R.sync, blockIdx.x, gridDim.x);
+        if (threadIdx.x == 0) arrive(R.sync, blockIdx.x, gridDim.x, R.meet_ticks);
     }
     constexpr bool COORDS = lds_coords(NPE, EPT);
     const int pid = xcd_block(blockIdx.x, gridDim.x), t = threadIdx.x;

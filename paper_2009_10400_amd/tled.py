@@ -121,6 +121,7 @@ _SIGS = {
     "tled_critical_dt": ([_P, _dp], ctypes.c_int),
     "tled_finalize": ([_P], ctypes.c_int),
     "tled_step": ([_P, _i64], ctypes.c_int),
+    "tled_resident_counts": ([_P, ctypes.POINTER(_i64), ctypes.POINTER(_i64)], ctypes.c_int),
     "tled_stream_copy": ([ctypes.c_int, _P, _P, ctypes.c_size_t, _P], ctypes.c_int),
     "tled_prepare_steps": ([_P, _i64], ctypes.c_int),
     "tled_sync": ([_P], ctypes.c_int),
@@ -333,6 +334,13 @@ class Sim:
     def prepare(self, n: int):
         """Capture the hipGraphs a following step(n) replays, without running anything."""
         self._check(_lib.tled_prepare_steps(self._h, int(n)))
+
+    def resident_counts(self):
+        """{"chunks", "given_up"}: chunks of steps enqueued in the resident kernel, and those of them that gave
+        up waiting for the GPU (done in another way, with the same results)."""
+        n, g = _i64(), _i64()
+        self._check(_lib.tled_resident_counts(self._h, ctypes.byref(n), ctypes.byref(g)))
+        return {"chunks": n.value, "given_up": g.value}
 
     def sync(self):
         self._check(_lib.tled_sync(self._h))
