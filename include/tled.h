@@ -256,10 +256,12 @@ tled_status tled_finalize(tled_sim *sim);
 tled_status tled_step(tled_sim *sim, int64_t n_steps);
 /* Small and medium problems (every patch of the mesh resident on the GPU at once, the
  * default kernels and shared_update 0) run chunks of four or more steps in one kernel.
- * chunks: those enqueued since tled_finalize; given_up: those among them whose workgroups
- * did not all come to run in time because others held the GPU, so that their steps were
- * done in another way (with the same results).  Either pointer may be NULL.  Waits for
- * the stream. */
+ * A chunk whose workgroups do not all come to run, because others hold the GPU, gives up
+ * after 20 ms (environment variable TLED_RESIDENT_WAIT_MS at tled_finalize, 0 to 1000;
+ * after 0.1 ms if the chunk before gave up too), and the workgroups that do run do its
+ * steps, with the same results.
+ * chunks: those enqueued since tled_finalize; given_up: those that gave up.  Either
+ * pointer may be NULL.  Waits for the stream. */
 tled_status tled_resident_counts(tled_sim *sim, int64_t *chunks, int64_t *given_up);
 /* Captures and instantiates, without running anything, the hipGraphs that a
  * following tled_step(sim, n_steps) replays: the chunk of graph_steps steps and

@@ -99,7 +99,7 @@ struct tled_sim {
     // are pa.partial and the shared tail of nu4, nv4)
     bool fuse = false;
     float4 *d_part2 = nullptr, *d_sux = nullptr, *d_svx = nullptr;
-    // chunks of steps in one kernel (resident.hip): on while no chunk has given up,
+    // chunks of steps in one kernel (resident.hip): whether they may run so,
     // patches that are resident at once, history steps held for the thermal dose
     bool resident = false;
     int res_cap = 0, hist_steps = 0;
@@ -372,6 +372,9 @@ void build_kernel_constants(tled_sim *s) {
     s->nparams = s->scen_np[0];
 }
 
+// Most workgroups that do the steps of a chunk that gave up: one per CU.
+int resident_team(int cus, int patches) { return std::max(1, std::min(cus, patches)); }
+
 // Whether chunks may run in the resident kernel: the default kernel variant with
 // 256-thread workgroups, its own order of launches not asked for (shared_update, the
 // persistent batch schedule), no anisotropy plane, elements that fit the kernel's one or
@@ -401,13 +404,15 @@ tled_status setup_resident(tled_sim *s) {
     ResidentArgs &r = s->ra;
     r = ResidentArgs{};
     // ticks of the 100 MHz clock before a chunk gives up waiting for all its workgroups
-    // to be resident: 20 ms, long against the kernels that usually share a GPU, short
-    // against what a user would notice once (TLED_RESIDENT_WAIT_MS)
+    // to be resident: 20 ms (TLED_RESIDENT_WAIT_MS), long against the kernels that usually
+    // share a GPU.  It is waited once: the chunks after one that gave up wait 0.1 ms at most
+    // (resident.hip), until one goes.
     const char *wait = std::getenv("TLED_RESIDENT_WAIT_MS");
     const double ms = wait ? std::atof(wait) : 20.0;
     r.meet_ticks = (long long)(1e5 * std::min(std::max(ms, 0.0), 1000.0));
     r.n_entries = int(P.shared_ids.size());
     r.nn = int(s->pc.nn);
+    r.team = resident_team(cus, P.n);
     std::vector<int32_t> sr(2 * P.shared_ids.size());
     for (size_t q = 0; q < P.shared_ids.size(); ++q) {
         const int64_t sn = P.shared_ids[q] - P.n_interior;
@@ -657,7 +662,9 @@ tled_status upload_all(tled_sim *s) {
             s->n_node_parts = P.n + s->q_sgrid;
         }
         TRY(zeros(s, &s->d_part_elem, s->n_elem_parts));
-        TRY(zeros(s, &s->d_part_node, size_t(4) * std::max(s->n_node_parts, P.n + 1)));
+        int cus = 0;
+        HIPCHK(s, hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, s->device));
+        TRY(zeros(s, &s->d_part_node, size_t(4) * std::max(s->n_node_parts, P.n + resident_team(cus, P.n))));
         a.part_elem = s->d_part_elem;
         a.part_node = s->d_part_node;
         // scenario tables
@@ -896,14 +903,9 @@ tled_status get_graph(tled_sim *s, int k, int64_t step0, hipGraphExec_t *out) {
 }
 
 tled_status check_status(tled_sim *s) {
-    unsigned st[2] = {0, 0};
-    HIPCHK(s, hipMemcpyAsync(st, s->d_status, sizeof(st), hipMemcpyDeviceToHost, s->stream));
+    unsigned flags = 0;
+    HIPCHK(s, hipMemcpyAsync(&flags, s->d_status, sizeof(unsigned), hipMemcpyDeviceToHost, s->stream));
     HIPCHK(s, hipStreamSynchronize(s->stream));
-    if (st[1] && s->resident) {   // chunks gave up (the GPU is shared): one launch per step from here on
-        s->resident = false;
-        drop_graphs(s);
-    }
-    const unsigned flags = st[0];
     if (flags) {
         std::string m = "device raised";
         if (flags & TLED_FLAG_NONFINITE) m += " non-finite values";

@@ -98,7 +98,7 @@ struct PatchArgs {
     float4 *su_out, *sv_out;
     const float4 *partial_prev;
     const long long *step_base;
-    unsigned *status;           // device flags; resident chunks that gave up
+    unsigned *status;           // device flags; count of resident chunks that gave up
     double *part_elem, *part_node;
     // scenario tables (a single problem is a batch of one scenario)
     const KMat *km;             // per scenario
@@ -124,11 +124,12 @@ struct ResidentArgs {
     int n_entries, nn;
     long long meet_ticks;       // of the 100 MHz clock: longest wait for all workgroups to be resident
     unsigned *sync;             // kResidentSyncWords: the meeting of a chunk's workgroups
+    int team;                   // most workgroups that do the steps of a chunk that gave up
     float *hist;                // temperature rise of every node after each step of the chunk, or null (no dose)
 };
 // Most Prony terms of the form with two elements per thread (its state is in registers).
 constexpr int kResidentMaxProny2 = 2;
-constexpr int kResidentSyncWords = 576;
+constexpr int kResidentSyncWords = 704;
 
 // Optional timing of one launch: both events are taken by the dispatch itself.
 struct LaunchTiming {

@@ -26,8 +26,13 @@
 // step they meet: the last to arrive decides GO; one that has waited meet_ticks decides
 // ABORT, and whichever came first holds for all (one compare-and-swap).
 // After ABORT every workgroup returns with the state untouched, and the finish kernel,
-// which ends every chunk, does the chunk's steps in its own single workgroup: slow,
-// and right whatever else occupies the GPU.  After GO each wait is for a workgroup
+// which ends every chunk, does the chunk's steps with those of its workgroups that have
+// come to run within 20 us (at least one, so it is right whatever else occupies the GPU):
+// they walk the patches and the shared nodes of a step together and meet twice per step.
+// From then on a chunk waits 0.1 ms at most, until one goes; nothing is asked of the host,
+// which may have enqueued any number of chunks by then.  (With the steps in a single
+// workgroup a chunk of 50 steps of the 83k-tet ellipsoid took 208 ms, 2.5 ms like this,
+// and every chunk waited meet_ticks anew.)  After GO each wait is for a workgroup
 // that runs, and that itself waits only for partials of earlier steps or of the same
 // step written before its own wait; a bound on the polls stays as a guard.
 //
@@ -41,6 +46,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "kernels.h"
 #include "step_math.h"
 
@@ -50,7 +57,16 @@ namespace {
 
 constexpr unsigned kGo = 1, kAbort = 2;
 constexpr int kMeetGroups = 16, kMeetStride = 32;   // words of 4 bytes: 128-byte lines
-static_assert(kMeetStride * (2 + kMeetGroups) == kResidentSyncWords, "decision, groups, arrivals per group");
+// Words of ResidentArgs::sync, each on a line of its own.  The meeting: the decision, groups
+// that are complete, arrivals per group; cleared by the finish kernel.  Its team after
+// ABORT: workgroups that joined (and kClosed), team size, arrivals at its barriers; cleared
+// by the next chunk's resident kernel.  kImpatient: the last chunk gave up.
+constexpr int kDecision = 0, kGroups = kMeetStride, kArrivals = 2 * kMeetStride,
+              kJoined = kArrivals + kMeetGroups * kMeetStride, kTeam = kJoined + kMeetStride,
+              kBarrier = kTeam + kMeetStride, kImpatient = kBarrier + kMeetStride;
+static_assert(kImpatient + kMeetStride == kResidentSyncWords, "one line per word");
+constexpr unsigned kClosed = 1u << 31;
+constexpr long long kShortTicks = 10000, kTeamTicks = 2000;   // 0.1 ms and 20 us of the 100 MHz clock
 constexpr unsigned kMaxPolls = 1u << 21;     // seconds; only a defect reaches it
 constexpr unsigned kEmpty = 0xffffffffu, kQuietNan = 0x7fc00000u;
 constexpr int kSc1 = 16;                     // cache policy of the buffer accesses: agent scope
@@ -76,6 +92,13 @@ struct Slots {
 // Waits until this wavefront's stores are complete.
 __device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
+__device__ __forceinline__ unsigned get_word(const unsigned *w) {
+    return __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void put_word(unsigned *w, unsigned v) {
+    __hip_atomic_store(w, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // Arrival at the meeting, thread 0: workgroup b of G counts itself in its group's word
 // (kMeetGroups words on lines of their own, since arrivals at one address are served one
 // after the other); each group's last counts the group, and the last group decides (with
@@ -83,22 +106,24 @@ __device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)
 __device__ __forceinline__ void arrive(unsigned *sync, unsigned b, unsigned G, long long ticks) {
     const unsigned g = b % kMeetGroups, groups = min(G, unsigned(kMeetGroups));
     const unsigned size = G / kMeetGroups + (g < G % kMeetGroups ? 1 : 0);
-    if (__hip_atomic_fetch_add(&sync[kMeetStride * (2 + g)], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 < size)
+    if (__hip_atomic_fetch_add(&sync[kArrivals + kMeetStride * g], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 < size)
         return;
-    if (__hip_atomic_fetch_add(&sync[kMeetStride], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 < groups) return;
+    if (__hip_atomic_fetch_add(&sync[kGroups], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 < groups) return;
     unsigned undecided = 0;
-    __hip_atomic_compare_exchange_strong(&sync[0], &undecided, ticks > 0 ? kGo : kAbort, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                         __HIP_MEMORY_SCOPE_AGENT);
+    if (__hip_atomic_compare_exchange_strong(&sync[kDecision], &undecided, ticks > 0 ? kGo : kAbort, __ATOMIC_RELAXED,
+                                             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+        put_word(sync + kImpatient, 0);
 }
 
 // Whether the launch's workgroups are all resident (the same answer for each), thread 0.
 __device__ __forceinline__ bool decided_go(unsigned *sync, long long ticks) {
     const long long t0 = wall_clock64();
     unsigned d;
-    while ((d = __hip_atomic_load(&sync[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) == 0) {
-        if (wall_clock64() - t0 >= ticks) {
+    while ((d = get_word(sync + kDecision)) == 0) {
+        const long long t = wall_clock64() - t0;
+        if (t >= ticks || (t >= kShortTicks && get_word(sync + kImpatient))) {
             unsigned undecided = 0;
-            __hip_atomic_compare_exchange_strong(&sync[0], &undecided, kAbort, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+            __hip_atomic_compare_exchange_strong(&sync[kDecision], &undecided, kAbort, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
                                                  __HIP_MEMORY_SCOPE_AGENT);
         } else {
             __builtin_amdgcn_s_sleep(2);
@@ -186,6 +211,11 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(NPE == 8
         const int p0 = xcd_block(blockIdx.x, gridDim.x);
         for (int q = A.shared_begin[p0] + int(threadIdx.x); q < A.shared_begin[p0 + 1]; q += kBlock)
             for (int b = 0; b < 3; ++b) x.put(u32x4{kEmpty, kEmpty, kEmpty, kEmpty}, b, A.ppos[q]);
+        if (blockIdx.x == 0 && threadIdx.x == 0) {   // the finish kernel of the chunk before is through
+            put_word(R.sync + kJoined, 0);
+            put_word(R.sync + kTeam, 0);
+            put_word(R.sync + kBarrier, 0);
+        }
         stores_done();
         __syncthreads();
         if (threadIdx.x == 0) arrive(R.sync, blockIdx.x, gridDim.x, R.meet_ticks);
@@ -256,6 +286,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(NPE == 8
     if (t == 0) go = decided_go(R.sync, R.meet_ticks);
     __syncthreads();
     if (!go) return;
+    // The loads above are complete from here on, for the compiler too: with one left that it
+    // may still have to wait for, it waits inside the loop, every step, and there for the
+    // step's stores as well (6000-tet cube 4.4 us per step, 4.0 like this).
+    __builtin_amdgcn_s_waitcnt(0x0f70);        // vmcnt(0)
     float psi = 0.f;
     bool nf = false, inv = false, lost = false;
     int b = 0;                                 // j mod 3
@@ -378,26 +412,83 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(NPE == 8
     }
 }
 
-// Ends a chunk of k steps over the first G patches: after ABORT does the steps, then
-// the monitor record, the step counter and the next launch's meeting words.
+// Barrier of the finish kernel's team of W running workgroups; n counts it.  The fences,
+// one wavefront's for its whole workgroup, make each workgroup's stores visible to the
+// others' loads after it.  lost: the guard on the polls has been reached.
+__device__ __forceinline__ void team_barrier(unsigned *arrivals, unsigned W, unsigned &n, bool &lost) {
+    stores_done();
+    __syncthreads();
+    ++n;
+    if (threadIdx.x == 0) {
+        __threadfence();
+        __hip_atomic_fetch_add(arrivals, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        unsigned polls = 0;
+        while (get_word(arrivals) < n * W && !lost) {
+            __builtin_amdgcn_s_sleep(2);
+            lost = ++polls >= kMaxPolls;
+        }
+        __threadfence();
+    }
+    __syncthreads();
+}
+
+// Joins the team that does the steps of a chunk that gave up, thread 0: this workgroup's
+// number in it and its size, which the first to come fixes when all have come or after
+// kTeamTicks.  False: too late.
+__device__ __forceinline__ bool join_team(unsigned *sync, unsigned all, unsigned &number, unsigned &size) {
+    number = __hip_atomic_fetch_add(&sync[kJoined], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (number & kClosed) return false;
+    if (number == 0) {
+        const long long t0 = wall_clock64();
+        while (get_word(sync + kJoined) < all && wall_clock64() - t0 < kTeamTicks) __builtin_amdgcn_s_sleep(2);
+        size = __hip_atomic_fetch_or(&sync[kJoined], kClosed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        put_word(sync + kTeam, size);
+    } else {
+        while ((size = get_word(sync + kTeam)) == 0) __builtin_amdgcn_s_sleep(2);
+    }
+    return true;
+}
+
+// Ends a chunk of k steps over the first G patches: after ABORT does the steps, with the
+// workgroups that run, then the monitor record, the step counter and the next launch's
+// meeting words.  After GO there is work for the first workgroup only.
 template <int NPE, int NP>
 __global__ __launch_bounds__(kBlock) void resident_finish_kernel(PatchArgs A, ResidentArgs R, int k, int G,
                                                                  long long *step_base, DevMonitors *mon) {
     extern __shared__ float4 lds[];
     __shared__ double shd[kBlock / 64];
     __shared__ float shf[kBlock / 64];
-    const bool aborted = uniform_int(reinterpret_cast<const int *>(&R.sync[0])) != int(kGo);
+    __shared__ unsigned number, size;
+    __shared__ bool joined;
+    // neither kGo nor kAbort: everything has been done and the word cleared
+    const unsigned decision = uniform_int(reinterpret_cast<const int *>(R.sync + kDecision));
+    if (decision != kAbort && (decision != kGo || blockIdx.x != 0)) return;
+    const bool aborted = decision == kAbort;
+    unsigned W = 1;
     if (aborted) {
+        if (threadIdx.x == 0) joined = join_team(R.sync, gridDim.x, number, size);
+        __syncthreads();
+        if (!joined) return;
+        const unsigned me = __builtin_amdgcn_readfirstlane(number);
+        W = __builtin_amdgcn_readfirstlane(size);
+        unsigned barriers = 0;
+        bool lost = false;
         const long long base = *A.step_base;
         for (int j = 0; j < k; ++j) {
-            for (int pid = 0; pid < G; ++pid)
-                patch_work<NPE, NP, true, kBlock, NPE == 4, true, kTi, true>(A, pid, j, lds, shd, shf);
-            __threadfence();
-            __syncthreads();
+            const bool last = j == k - 1;
+            for (int pid = int(me); pid < G; pid += int(W)) {
+                if (last) patch_work<NPE, NP, true, kBlock, NPE == 4, true, kTi, true>(A, pid, j, lds, shd, shf);
+                else patch_work<NPE, NP, false, kBlock, NPE == 4, true, kTi, true>(A, pid, j, lds, shd, shf);
+                __syncthreads();
+                if (R.hist)
+                    for (int a = A.int_begin[pid] + int(threadIdx.x); a < A.int_begin[pid + 1]; a += kBlock)
+                        R.hist[size_t(j) * R.nn + a] = A.nu4[a].w;
+            }
+            team_barrier(R.sync + kBarrier, W, barriers, lost);
             NodeMon mo{0.0, -INFINITY, INFINITY, 0.0};
             bool nf = false;
             const long long step = base + j;
-            for (int s = threadIdx.x; s < A.n_shared; s += kBlock) {
+            for (int s = int(me) * kBlock + int(threadIdx.x); s < A.n_shared; s += int(W) * kBlock) {
                 const int sc = A.shared_scen[s];
                 if (step >= A.scen_end[sc]) continue;
                 const NodeParams p = A.np[sc];
@@ -408,22 +499,22 @@ __global__ __launch_bounds__(kBlock) void resident_finish_kernel(PatchArgs A, Re
                 A.nu4[a] = r.u;
                 A.nv4[a] = r.v;
                 nf |= r.nonfinite;
+                if (R.hist) R.hist[size_t(j) * R.nn + a] = r.u.w;
                 node_monitor(p, r, A.Vl[a], mo);
             }
-            raise_flags(A.status, nf, false);
-            __threadfence();
-            __syncthreads();
-            if (R.hist)
-                for (int a = threadIdx.x; a < R.nn; a += kBlock) R.hist[size_t(j) * R.nn + a] = A.nu4[a].w;
-            write_node_partials<kBlock>(mo, A.part_node, G, shd, shf);
+            raise_flags(A.status, nf || lost, false);
+            if (last) write_node_partials<kBlock>(mo, A.part_node, G + int(me), shd, shf);
+            team_barrier(R.sync + kBarrier, W, barriers, lost);
         }
-        __threadfence();
-        __syncthreads();
+        if (me != 0) return;
     }
-    finish_monitors(A.part_elem, G, A.part_node, G + 1, step_base, k, A.status, mon, shd, shf);
+    finish_monitors(A.part_elem, G, A.part_node, G + int(W), step_base, k, A.status, mon, shd, shf);
     __syncthreads();
-    for (int i = threadIdx.x; i < kResidentSyncWords; i += kBlock) R.sync[i] = 0;
-    if (threadIdx.x == 0 && aborted) A.status[1] += 1;
+    if (threadIdx.x < kJoined / kMeetStride) put_word(R.sync + kMeetStride * threadIdx.x, 0);
+    if (threadIdx.x == 0 && aborted) {
+        A.status[1] += 1;
+        put_word(R.sync + kImpatient, 1);
+    }
 }
 
 // Thermal dose of a chunk from its temperature history, step by step as dose_kernel.
@@ -478,8 +569,8 @@ void finish_npe(int np, const PatchArgs &a, const ResidentArgs &r, int k, long l
                 hipStream_t s) {
     const size_t lds = patch_lds_bytes(NPE, NPE == 4, a);
 #define TLED_RF(NPV)                                                                                              \
-    hipLaunchKernelGGL((resident_finish_kernel<NPE, NPV>), dim3(1), dim3(kBlock), lds, s, a, r, k, a.n_patches, \
-                       step_base, mon)
+    hipLaunchKernelGGL((resident_finish_kernel<NPE, NPV>), dim3(std::min(a.n_patches, r.team)), dim3(kBlock), lds, s, a, r, \
+                       k, a.n_patches, step_base, mon)
     switch (np) {
         case 0: TLED_RF(0); break;
         case 1: TLED_RF(1); break;
