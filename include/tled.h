@@ -259,7 +259,9 @@ tled_status tled_step(tled_sim *sim, int64_t n_steps);
  * A chunk whose workgroups do not all come to run, because others hold the GPU, gives up
  * after 20 ms (environment variable TLED_RESIDENT_WAIT_MS at tled_finalize, 0 to 1000;
  * after 0.1 ms if the chunk before gave up too), and the workgroups that do run do its
- * steps, with the same results.
+ * steps, with the same results.  Handles of one process on streams of their own run such
+ * chunks side by side where they fit on the GPU together; where they do not, their chunks
+ * are launched step by step, which overlaps, until fewer of them are under way.
  * chunks: those enqueued since tled_finalize; given_up: those that gave up.  Either
  * pointer may be NULL.  Waits for the stream. */
 tled_status tled_resident_counts(tled_sim *sim, int64_t *chunks, int64_t *given_up);

@@ -25,6 +25,18 @@ namespace {
 
 constexpr uint64_t kStateMagic = 0x31534544454c5454ULL;  // "TTLEDES1"
 
+// The handles of one device whose chunks may run in the resident kernel.  Two such kernels
+// at once need all their workgroups resident together, or each could hold part of the CUs
+// and wait for the rest (they give up after a while, which is right but slow).  So a chunk
+// runs in the resident kernel only when it fits beside those of the others that may still
+// be running on other streams; else it takes the per-step launches, which overlap with
+// anything.  (Two 6000-tet cubes, a stream each: 4.7 us per step of both; one after the
+// other 9.0; with per-step launches 8.5.)
+struct ResidentDevice {
+    std::mutex mu;
+    std::vector<tled_sim *> sims;
+};
+
 struct DevBuf {
     void *p = nullptr;
     size_t bytes = 0;
@@ -104,8 +116,13 @@ struct tled_sim {
     bool resident = false;
     int res_cap = 0, hist_steps = 0;
     ResidentArgs ra{};
-    hipEvent_t res_ev = nullptr;
     int64_t res_chunks = 0;            // run in the resident kernel since finalize
+    // among the handles of the device: chunks launched and (pinned host memory, written by the
+    // chunks) done, modulo 2^32, and the part of the GPU that the last one takes
+    ResidentDevice *res_dev = nullptr;
+    unsigned res_launched = 0;
+    volatile unsigned *res_done = nullptr;
+    double res_share = 0.0;
     // thermal dose (tled_set_thermal_dose): per node (CEM43 minutes, Arrhenius integral)
     bool dose_on = false;
     double dose_A = 0.0, dose_Ea = 0.0;
@@ -165,17 +182,8 @@ int patch_mode(const tled_sim *s) {
     return mode;
 }
 
-// Resident chunks of one device run one after the other, also from several handles,
-// streams and threads: two at once could each hold part of the CUs and wait for the
-// rest (the kernels give such a chunk up after a while, which is right but slow).
-// Handles register at finalize; a launch by another handle than the last one waits for
-// that one's event, recorded after each launch while more than one handle is registered.
-struct ResidentOrder {
-    int users = 0;
-    tled_sim *last = nullptr;
-};
 std::mutex g_resident_mu;
-std::map<int, ResidentOrder> g_resident;   // by device ordinal
+std::map<int, ResidentDevice> g_resident;   // by device ordinal; entries stay
 
 tled_status fail(tled_sim *s, tled_status st, const std::string &msg) {
     if (s) s->err = msg;
@@ -215,49 +223,72 @@ void release_bufs(tled_sim *s, size_t keep) {
     s->bufs.resize(keep);
 }
 
-tled_status resident_register(tled_sim *s) {
-    HIPCHK(s, hipEventCreateWithFlags(&s->res_ev, hipEventDisableTiming));
-    std::lock_guard<std::mutex> lock(g_resident_mu);
-    ResidentOrder &o = g_resident[s->device];
-    if (o.users == 1 && o.last) HIPCHK(s, hipEventRecord(o.last->res_ev, o.last->stream));
-    ++o.users;
-    return TLED_OK;
+// False: no host memory to hear from the chunks, so no resident chunks.
+bool resident_register(tled_sim *s) {
+    void *h = nullptr, *d = nullptr;
+    if (hipHostMalloc(&h, sizeof(unsigned), hipHostMallocDefault) != hipSuccess ||
+        hipHostGetDevicePointer(&d, h, 0) != hipSuccess) {
+        if (h) (void)hipHostFree(h);
+        (void)hipGetLastError();
+        return false;
+    }
+    s->res_done = static_cast<volatile unsigned *>(h);
+    *s->res_done = 0;
+    s->ra.done = static_cast<unsigned *>(d);
+    {
+        std::lock_guard<std::mutex> lock(g_resident_mu);
+        s->res_dev = &g_resident[s->device];
+    }
+    std::lock_guard<std::mutex> lock(s->res_dev->mu);
+    s->res_dev->sims.push_back(s);
+    return true;
 }
 
 // After the handle's stream has been synchronised.
 void resident_unregister(tled_sim *s) {
-    if (!s->res_ev) return;
+    if (!s->res_dev) return;
     {
-        std::lock_guard<std::mutex> lock(g_resident_mu);
-        ResidentOrder &o = g_resident[s->device];
-        if (o.last == s) o.last = nullptr;
-        --o.users;
+        std::lock_guard<std::mutex> lock(s->res_dev->mu);
+        auto &v = s->res_dev->sims;
+        v.erase(std::find(v.begin(), v.end(), s));
     }
-    (void)hipEventDestroy(s->res_ev);
-    s->res_ev = nullptr;
+    s->res_dev = nullptr;
+    (void)hipHostFree(const_cast<unsigned *>(s->res_done));
+    s->res_done = nullptr;
 }
 
-// Holds the device's order of resident chunks over the launches of one call.
-class ResidentTurn {
+// One chunk among those of the other handles: counted as launched until it says in host
+// memory that it has ended (an event would have to be asked for, which is an error and ends
+// the capture when the stream it was recorded on is being captured), and granted the
+// resident kernel or not.  Chunks that run by steps count as well, so that of several
+// problems that do not fit together all run by steps (three 83k-tet ellipsoids 13.6 us per
+// step of all; with one of them resident 15.7).  Those of a batch too large for the resident
+// kernel do not: next to them it is the better way.
+class ResidentPlace {
 public:
-    explicit ResidentTurn(tled_sim *s) : s_(s) {
-        if (!s->resident) return;
-        lock_ = std::unique_lock<std::mutex>(g_resident_mu);
-        const ResidentOrder &o = g_resident[s->device];
-        if (o.last && o.last != s) err_ = hipStreamWaitEvent(s->stream, o.last->res_ev, 0);
+    // may: whether the chunk, over np patches, may run in the resident kernel
+    ResidentPlace(tled_sim *s, int np, bool may) : s_(s) {
+        std::lock_guard<std::mutex> lock(s->res_dev->mu);
+        double load = double(np) / s->res_cap;
+        s->res_share = load;
+        for (const tled_sim *o : s->res_dev->sims)
+            // work on the same stream comes one after the other
+            if (o != s && o->stream != s->stream && *o->res_done != o->res_launched && o->res_share <= 1.0)
+                load += o->res_share;
+        granted_ = may && load <= 1.0;
+        ++s->res_launched;
     }
-    hipError_t error() const { return err_; }
-    ~ResidentTurn() {
-        if (!lock_.owns_lock()) return;
-        ResidentOrder &o = g_resident[s_->device];
-        if (o.users > 1) (void)hipEventRecord(s_->res_ev, s_->stream);
-        o.last = s_;
+    bool granted() const { return granted_; }
+    void launched() { s_ = nullptr; }
+    ~ResidentPlace() {                            // without a launch nothing will say that it has ended
+        if (!s_) return;
+        std::lock_guard<std::mutex> lock(s_->res_dev->mu);
+        --s_->res_launched;
     }
 
 private:
     tled_sim *s_;
-    std::unique_lock<std::mutex> lock_;
-    hipError_t err_ = hipSuccess;
+    bool granted_ = false;
 };
 
 void drop_graphs(tled_sim *s) {
@@ -426,7 +457,7 @@ tled_status setup_resident(tled_sim *s) {
     r.xbuf = dsr ? static_cast<float4 *>(dev_alloc(s, sizeof(float4) * 3 * size_t(r.n_entries))) : nullptr;
     r.sync = r.xbuf ? static_cast<unsigned *>(dev_alloc(s, sizeof(unsigned) * kResidentSyncWords)) : nullptr;
     if (r.sync && s->dose_on) r.hist = static_cast<float *>(dev_alloc(s, sizeof(float) * hist_steps * size_t(r.nn)));
-    if (!r.sync || (s->dose_on && !r.hist)) {
+    if (!r.sync || (s->dose_on && !r.hist) || !resident_register(s)) {
         release_bufs(s, held);
         (void)hipGetLastError();                  // a failed hipMalloc's, or the next launch would report it
         r = ResidentArgs{};
@@ -437,7 +468,6 @@ tled_status setup_resident(tled_sim *s) {
     HIPCHK(s, hipMemcpyAsync(dsr, sr.data(), sizeof(int32_t) * sr.size(), hipMemcpyHostToDevice, s->stream));
     HIPCHK(s, hipMemsetAsync(r.sync, 0, sizeof(unsigned) * kResidentSyncWords, s->stream));
     HIPCHK(s, hipStreamSynchronize(s->stream));   // sr is uploaded asynchronously
-    TRY(resident_register(s));
     s->resident = true;
     return TLED_OK;
 }
@@ -757,23 +787,20 @@ tled_status set_queue_counts(tled_sim *s, int64_t step, long long h[2]) {
 // With ev (4 events per step + 2): the element/patch and node/shared-node
 // launches of step j carry the pairs (4j, 4j+1) and (4j+2, 4j+3), taken by the
 // dispatches themselves; the finish kernel is bracketed by the last two.
-tled_status enqueue_chunk(tled_sim *s, int k, int64_t step0, bool captured,
+// resident: in the resident kernel (resident_chunk holds).  counted: the chunk's end is
+// reported in host memory (ResidentPlace).
+tled_status enqueue_chunk(tled_sim *s, int k, int64_t step0, bool captured, bool resident, bool counted,
                           std::vector<hipEvent_t> *ev = nullptr) {
     const int npe = s->pc.npe;
     const int bs = s->opt.block_size > 0 ? s->opt.block_size : kBlock;
-    if (!ev && s->resident) {
+    if (resident) {
         PatchArgs pa = s->pa;
-        if (s->is_batch) {
-            int64_t ns;
-            active_counts(s, step0, &pa.n_patches, &ns);
-            pa.n_shared = int(ns);
-        }
-        if (resident_chunk(s, k, pa.n_patches)) {
-            launch_resident(npe, s->np, pa, s->ra, k, s->d_step, s->d_mon, s->d_dose, s->dq, s->stream);
-            HIPCHK(s, hipGetLastError());
-            if (!captured) ++s->res_chunks;
-            return TLED_OK;
-        }
+        int64_t ns;
+        active_counts(s, step0, &pa.n_patches, &ns);
+        pa.n_shared = int(ns);
+        launch_resident(npe, s->np, pa, s->ra, k, s->d_step, s->d_mon, s->d_dose, s->dq, s->stream);
+        HIPCHK(s, hipGetLastError());
+        return TLED_OK;
     }
     for (int j = 0; j < k; ++j) {
         const bool mon = (j == k - 1);
@@ -833,7 +860,7 @@ tled_status enqueue_chunk(tled_sim *s, int k, int64_t step0, bool captured,
     }
     if (ev) HIPCHK(s, hipEventRecord((*ev)[4 * size_t(k)], s->stream));
     launch_finish(s->d_part_elem, s->n_elem_parts, s->d_part_node, s->n_node_parts, s->d_step, k, s->d_status,
-                  s->d_mon, s->stream);
+                  s->d_mon, counted ? s->ra.sync : nullptr, s->ra.done, s->stream);
     if (ev) HIPCHK(s, hipEventRecord((*ev)[4 * size_t(k) + 1], s->stream));
     HIPCHK(s, hipGetLastError());
     return TLED_OK;
@@ -841,23 +868,23 @@ tled_status enqueue_chunk(tled_sim *s, int k, int64_t step0, bool captured,
 
 constexpr size_t kMaxGraphs = 8;
 
-// The cached graph of a k-step chunk starting at step0, or null.
-hipGraphExec_t find_graph(tled_sim *s, int k, int64_t step0) {
+// The cached graph of a k-step chunk starting at step0 in the resident kernel or by steps, or null.
+hipGraphExec_t find_graph(tled_sim *s, int k, int64_t step0, bool resident) {
     int np;
     int64_t ns;
     active_counts(s, step0, &np, &ns);
     for (auto &g : s->graphs)
-        if (g.k == k && g.np == np && g.ns == ns) {
+        if (g.k == k && g.np == np && g.ns == ns && g.resident == resident) {
             g.used = ++s->graph_clock;
             return g.exec;
         }
     return nullptr;
 }
 
-tled_status build_graph(tled_sim *s, int k, int64_t step0, hipGraphExec_t *out) {
+tled_status build_graph(tled_sim *s, int k, int64_t step0, bool resident, hipGraphExec_t *out) {
     hipGraph_t g = nullptr;
     HIPCHK(s, hipStreamBeginCapture(s->stream, hipStreamCaptureModeThreadLocal));
-    tled_status st = enqueue_chunk(s, k, step0, true);
+    tled_status st = enqueue_chunk(s, k, step0, true, resident, s->res_dev != nullptr);
     hipError_t e = hipStreamEndCapture(s->stream, &g);
     if (st != TLED_OK) {
         if (g) (void)hipGraphDestroy(g);
@@ -882,24 +909,57 @@ tled_status build_graph(tled_sim *s, int k, int64_t step0, hipGraphExec_t *out) 
         (void)hipGraphExecDestroy(lru->exec);
         s->graphs.erase(lru);
     }
-    tled_sim::GraphEntry ge{exec, k, 0, 0, ++s->graph_clock, false};
+    tled_sim::GraphEntry ge{exec, k, 0, 0, ++s->graph_clock, resident};
     active_counts(s, step0, &ge.np, &ge.ns);
-    ge.resident = resident_chunk(s, k, ge.np);
     s->graphs.push_back(ge);
     *out = exec;
     return TLED_OK;
 }
 
-tled_status launch_graph(tled_sim *s, hipGraphExec_t g) {
-    HIPCHK(s, hipGraphLaunch(g, s->stream));
-    for (const auto &e : s->graphs)
-        if (e.exec == g && e.resident) ++s->res_chunks;
-    return TLED_OK;
+tled_status get_graph(tled_sim *s, int k, int64_t step0, bool resident, hipGraphExec_t *out) {
+    *out = find_graph(s, k, step0, resident);
+    return *out ? TLED_OK : build_graph(s, k, step0, resident, out);
 }
 
-tled_status get_graph(tled_sim *s, int k, int64_t step0, hipGraphExec_t *out) {
-    *out = find_graph(s, k, step0);
-    return *out ? TLED_OK : build_graph(s, k, step0, out);
+// Whether the k-step chunk that starts at step0 may run in the resident kernel.
+bool may_be_resident(const tled_sim *s, int k, int64_t step0) {
+    int np;
+    int64_t ns;
+    active_counts(s, step0, &np, &ns);
+    return resident_chunk(s, k, np);
+}
+
+// The chunk of k steps from step0: a whole chunk (graph_steps) replays its graph; a shorter
+// one does when a graph of its length is cached (tled_prepare_steps captures it), else it is
+// enqueued eagerly.
+tled_status run_chunk(tled_sim *s, int k, int64_t step0, bool capturing) {
+    auto graph = [&](bool resident, hipGraphExec_t *g) -> tled_status {
+        *g = nullptr;
+        if (s->opt.graph_steps <= 0) return TLED_OK;
+        if (k == s->opt.graph_steps) return get_graph(s, k, step0, resident, g);
+        if (!capturing) *g = find_graph(s, k, step0, resident);
+        return TLED_OK;
+    };
+    auto launch = [&](bool resident, hipGraphExec_t g) -> tled_status {
+        if (!g) return enqueue_chunk(s, k, step0, false, resident, s->res_dev && !capturing);
+        HIPCHK(s, hipGraphLaunch(g, s->stream));
+        return TLED_OK;
+    };
+    hipGraphExec_t g;
+    if (!s->res_dev || capturing) {
+        TRY(graph(false, &g));
+        return launch(false, g);
+    }
+    int np;
+    int64_t ns;
+    active_counts(s, step0, &np, &ns);
+    ResidentPlace place(s, np, resident_chunk(s, k, np));
+    const bool resident = place.granted();
+    TRY(graph(resident, &g));
+    TRY(launch(resident, g));
+    place.launched();
+    if (resident) ++s->res_chunks;
+    return TLED_OK;
 }
 
 tled_status check_status(tled_sim *s) {
@@ -1253,43 +1313,14 @@ tled_status tled_resident_counts(tled_sim *sim, int64_t *chunks, int64_t *given_
 tled_status tled_step(tled_sim *sim, int64_t n_steps) {
     TRY(need_device(sim));
     if (n_steps < 0) return fail(sim, TLED_E_ARG, "negative step count");
-    const int k = sim->opt.graph_steps;
-    int64_t left = n_steps, cur = sim->step;
     if (n_steps == 0) return TLED_OK;
     // a stream that its owner is capturing takes the launches of single steps
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     if (sim->resident) HIPCHK(sim, hipStreamIsCapturing(sim->stream, &capture));
-    struct Restore {
-        bool &flag, value;
-        ~Restore() { flag = value; }
-    } restore{sim->resident, sim->resident};
-    if (capture != hipStreamCaptureStatusNone) sim->resident = false;
-    ResidentTurn turn(sim);
-    HIPCHK(sim, turn.error());
-    if (k > 0) {
-        while (left >= k) {
-            // a batch's graph launches the prefix of scenarios running at its
-            // first step: captured again when that prefix has changed
-            hipGraphExec_t g;
-            TRY(get_graph(sim, k, cur, &g));
-            TRY(launch_graph(sim, g));
-            left -= k;
-            cur += k;
-        }
-        // a shorter last chunk replays a graph of its length when one is cached
-        // (tled_prepare_steps captures it), else it is enqueued eagerly
-        if (left > 0) {
-            if (hipGraphExec_t g = find_graph(sim, int(left), cur)) {
-                TRY(launch_graph(sim, g));
-                cur += left;
-                left = 0;
-            }
-        }
-    }
-    const int chunk = k > 0 ? k : 100;
-    while (left > 0) {
-        int c = int(std::min<int64_t>(left, chunk));
-        TRY(enqueue_chunk(sim, c, cur, false));
+    const int chunk = sim->opt.graph_steps > 0 ? sim->opt.graph_steps : 100;
+    for (int64_t left = n_steps, cur = sim->step; left > 0;) {
+        const int c = int(std::min<int64_t>(left, chunk));
+        TRY(run_chunk(sim, c, cur, capture != hipStreamCaptureStatusNone));
         left -= c;
         cur += c;
     }
@@ -1305,10 +1336,11 @@ tled_status tled_prepare_steps(tled_sim *sim, int64_t n_steps) {
     hipGraphExec_t g;
     const int64_t full = n_steps / k, rest = n_steps % k;
     int64_t cur = sim->step;
-    if (full > 0) TRY(get_graph(sim, k, cur, &g));
+    if (full > 0) TRY(get_graph(sim, k, cur, may_be_resident(sim, k, cur), &g));
     if (rest > 0) {
         // a batch's prefix may differ at the last chunk: capture at the step it starts
-        TRY(get_graph(sim, int(rest), cur + full * k, &g));
+        const int64_t at = cur + full * k;
+        TRY(get_graph(sim, int(rest), at, may_be_resident(sim, int(rest), at), &g));
     }
     return TLED_OK;
 }
@@ -1867,7 +1899,7 @@ tled_status tled_kernel_times(tled_sim *sim, int64_t n_steps, double ms[3]) {
     tled_status st = TLED_OK;
     while (left > 0 && st == TLED_OK) {
         int c = int(std::min<int64_t>(left, chunk));
-        st = enqueue_chunk(sim, c, cur, false, &ev);
+        st = enqueue_chunk(sim, c, cur, false, false, false, &ev);
         if (st != TLED_OK) break;
         HIPCHK(sim, hipStreamSynchronize(sim->stream));
         for (int j = 0; j < c; ++j) {

@@ -124,12 +124,14 @@ struct ResidentArgs {
     int n_entries, nn;
     long long meet_ticks;       // of the 100 MHz clock: longest wait for all workgroups to be resident
     unsigned *sync;             // kResidentSyncWords: the meeting of a chunk's workgroups
+    unsigned *done;             // host memory: chunks that have ended, modulo 2^32
     int team;                   // most workgroups that do the steps of a chunk that gave up
     float *hist;                // temperature rise of every node after each step of the chunk, or null (no dose)
 };
 // Most Prony terms of the form with two elements per thread (its state is in registers).
 constexpr int kResidentMaxProny2 = 2;
-constexpr int kResidentSyncWords = 704;
+constexpr int kResidentSyncWords = 736;
+constexpr int kResidentEnded = 704;   // the word of sync that counts the chunks that have ended
 
 // Optional timing of one launch: both events are taken by the dispatch itself.
 struct LaunchTiming {
@@ -167,7 +169,8 @@ void launch_scenario_monitors(const float4 *nu4, const float *Vl, const long lon
                               const NodeParams *np, int n_scen, float T_abl, double *out /* 2 per scenario */,
                               hipStream_t s);
 void launch_finish(const double *part_elem, int n_elem_parts, const double *part_node, int n_node_parts,
-                   long long *step_base, int k, const unsigned *status, DevMonitors *mon, hipStream_t s);
+                   long long *step_base, int k, const unsigned *status, DevMonitors *mon, unsigned *sync,
+                   unsigned *done, hipStream_t s);   // sync, done: of ResidentArgs; sync null: not counted
 size_t patch_lds_bytes(int npe, bool geox, const PatchArgs &a);
 // k steps over the first a.n_patches patches and a.n_shared shared nodes in one
 // launch, then the kernel that ends the chunk (default kernel variants: T4 with

@@ -262,10 +262,11 @@ __global__ __launch_bounds__(kBlock) void shared_node_queue_kernel(PatchArgs A, 
 __global__ __launch_bounds__(kBlock) void finish_kernel(const double *__restrict__ part_elem, int n_elem_parts,
                                                         const double *__restrict__ part_node, int n_node_parts,
                                                         long long *step_base, int k, const unsigned *status,
-                                                        DevMonitors *mon) {
+                                                        DevMonitors *mon, unsigned *sync, unsigned *done) {
     __shared__ double shd[kBlock / 64];
     __shared__ float shf[kBlock / 64];
     finish_monitors(part_elem, n_elem_parts, part_node, n_node_parts, step_base, k, status, mon, shd, shf);
+    if (sync && threadIdx.x == 0) count_chunk(sync, done);
 }
 
 // ---------------------------------------------------------------- launchers
@@ -528,9 +529,10 @@ void launch_scenario_monitors(const float4 *nu4, const float *Vl, const long lon
 }
 
 void launch_finish(const double *part_elem, int n_elem_parts, const double *part_node, int n_node_parts,
-                   long long *step_base, int k, const unsigned *status, DevMonitors *mon, hipStream_t s) {
+                   long long *step_base, int k, const unsigned *status, DevMonitors *mon, unsigned *sync,
+                   unsigned *done, hipStream_t s) {
     hipLaunchKernelGGL(finish_kernel, dim3(1), dim3(kBlock), 0, s, part_elem, n_elem_parts, part_node, n_node_parts,
-                       step_base, k, status, mon);
+                       step_base, k, status, mon, sync, done);
 }
 
 size_t patch_lds_bytes(int npe, bool geox, const PatchArgs &a) {

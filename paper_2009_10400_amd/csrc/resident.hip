@@ -60,11 +60,13 @@ constexpr int kMeetGroups = 16, kMeetStride = 32;   // words of 4 bytes: 128-byt
 // Words of ResidentArgs::sync, each on a line of its own.  The meeting: the decision, groups
 // that are complete, arrivals per group; cleared by the finish kernel.  Its team after
 // ABORT: workgroups that joined (and kClosed), team size, arrivals at its barriers; cleared
-// by the next chunk's resident kernel.  kImpatient: the last chunk gave up.
+// by the next chunk's resident kernel.  kImpatient: the last chunk gave up.  kEnded: chunks
+// that have ended.
 constexpr int kDecision = 0, kGroups = kMeetStride, kArrivals = 2 * kMeetStride,
               kJoined = kArrivals + kMeetGroups * kMeetStride, kTeam = kJoined + kMeetStride,
-              kBarrier = kTeam + kMeetStride, kImpatient = kBarrier + kMeetStride;
-static_assert(kImpatient + kMeetStride == kResidentSyncWords, "one line per word");
+              kBarrier = kTeam + kMeetStride, kImpatient = kBarrier + kMeetStride,
+              kEnded = kImpatient + kMeetStride;
+static_assert(kEnded == kResidentEnded && kEnded + kMeetStride == kResidentSyncWords, "one line per word");
 constexpr unsigned kClosed = 1u << 31;
 constexpr long long kShortTicks = 10000, kTeamTicks = 2000;   // 0.1 ms and 20 us of the 100 MHz clock
 constexpr unsigned kMaxPolls = 1u << 21;     // seconds; only a defect reaches it
@@ -511,9 +513,12 @@ __global__ __launch_bounds__(kBlock) void resident_finish_kernel(PatchArgs A, Re
     finish_monitors(A.part_elem, G, A.part_node, G + int(W), step_base, k, A.status, mon, shd, shf);
     __syncthreads();
     if (threadIdx.x < kJoined / kMeetStride) put_word(R.sync + kMeetStride * threadIdx.x, 0);
-    if (threadIdx.x == 0 && aborted) {
-        A.status[1] += 1;
-        put_word(R.sync + kImpatient, 1);
+    if (threadIdx.x == 0) {
+        if (aborted) {
+            A.status[1] += 1;
+            put_word(R.sync + kImpatient, 1);
+        }
+        count_chunk(R.sync, R.done);
     }
 }
 

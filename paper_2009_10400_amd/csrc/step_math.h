@@ -706,6 +706,13 @@ __device__ __forceinline__ void patch_work(const PatchArgs &A, const int pid, co
     }
 }
 
+// A chunk has ended, one thread: counted, and reported to the host.
+__device__ __forceinline__ void count_chunk(unsigned *sync, unsigned *done) {
+    const unsigned n = sync[kResidentEnded] + 1;
+    sync[kResidentEnded] = n;
+    __hip_atomic_store(done, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // One block: sums the per-block partials in a fixed order, writes the monitor
 // record and advances the device step counter by the chunk length.
 __device__ __forceinline__ void finish_monitors(const double *part_elem, int n_elem_parts, const double *part_node,
