@@ -367,9 +367,12 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(NPE == 8
         }
         // Not too early: a poll that comes before its partials costs a whole round trip, and
         // polls delay the stores they wait for.  With many workgroups the first poll waits
-        // until this one's own partials are through and a little longer (83k-tet ellipsoid,
-        // 648 workgroups: 8.3 us per step without, 6.1 with); with few it goes out at once
-        // (6000-tet cube, 47: 4.0 and 4.2).
+        // until this one's own partials are through and a little longer, with few it goes out
+        // at once.  us per step, at once / waiting: T4 with 47 workgroups 4.14 / 4.41, 81 4.15 /
+        // 4.36, 102 4.71 / 4.70, 126 4.73 / 4.70, 159 4.50 / 4.28, 203 5.08 / 4.74, 431 6.96 /
+        // 5.50, 650 8.51 / 6.47, 1018 10.1 / 7.3; two elements per thread with 68 6.32 / 6.68,
+        // 135 6.71 / 7.01, 201 7.12 / 6.73, 448 11.2 / 10.2.  H8, where a step is longer, loses
+        // little by either: 77 6.34 / 6.92, 154 6.46 / 6.79, 250 7.10 / 7.13, 489 9.34 / 9.32.
         if (gridDim.x > 128) {
             __builtin_amdgcn_s_sleep(16);
             stores_done();
