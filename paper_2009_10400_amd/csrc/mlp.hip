@@ -241,7 +241,7 @@ __device__ inline void tile_of_block(int &bx, int &by, int &bz) {
     bz = H / (nx * ny);
 }
 
-// C = A B with A(m,k) = A[m*sam + k*sak], B(k,n) = B[k*sbk + n*sbn] (bfloat16 bits).
+// C = A B with A(m,k) = A[m*lda + k], B(k,n) = B[k*sbk + n*sbn] (bfloat16 bits).
 // 64x64 output tile per workgroup of four wavefronts, each wavefront 32x32 as
 // 2x2 MFMA 16x16x32 tiles.  Lane l of a 16x16x32 MFMA supplies A[l%16][8(l/16)..+7]
 // and B[8(l/16)..+7][l%16] and receives D[4(l/16)+r][l%16], r = 0..3.  k runs in
@@ -258,10 +258,11 @@ __device__ inline void tile_of_block(int &bx, int &by, int &bz) {
 // latency (64-68 VGPRs with the staged values packed two per register).
 template <int EPI, int AM, int BMODE>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) void gemm_kernel(
-    int M, int N, int K, const uint16_t *__restrict__ A, long sam, long sak, const uint16_t *__restrict__ B, long sbk,
+    int M, int N, int K, const uint16_t *__restrict__ A, long lda, const uint16_t *__restrict__ B, long sbk,
     long sbn, float *__restrict__ C, long scm, long scn, uint16_t *__restrict__ Act, const float *__restrict__ bias,
     int kchunk) {
-    static_assert(BM == BK && BN == BK, "a k-major tile reuses the r-major tile's array");
+    static_assert(AM != LD_RVEC, "A has its rows along k");
+    static_assert(BN == BK, "a k-major tile of B reuses the r-major tile's array");
     __shared__ __attribute__((aligned(16))) uint16_t As[2][BM][BKP];
     __shared__ __attribute__((aligned(16))) uint16_t Bt[2][BN][BKP];
     int bx, by, bz;
@@ -283,7 +284,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
     if (ntiles > 0) {
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-            tile_load<AM>(qa[h], A, sam, sak, m0, M, kb, ke, t, h);
+            tile_load<AM>(qa[h], A, lda, 1, m0, M, kb, ke, t, h);
             tile_load<BMODE>(qb[h], B, sbn, sbk, n0, N, kb, ke, t, h);
             tile_store<AM>(qa[h], &As[0][0][0], BKP, 0, t, h);
             tile_store<BMODE>(qb[h], &Bt[0][0][0], BKP, 0, t, h);
@@ -296,7 +297,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
         if (more) {
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
-                tile_load<AM>(qa[h], A, sam, sak, m0, M, k0 + BK, ke, t, h);
+                tile_load<AM>(qa[h], A, lda, 1, m0, M, k0 + BK, ke, t, h);
                 tile_load<BMODE>(qb[h], B, sbn, sbk, n0, N, k0 + BK, ke, t, h);
             }
         }
@@ -1420,7 +1421,7 @@ int load_mode(const uint16_t *X, long sr, long sk) {
 // buffer, grown on demand.  Split-K (EPI_F32, fewer than 256 output tiles): about 512
 // workgroups (nz x tiles), at most 64 k chunks.
 template <int EPI>
-tled_status gemm(tled_mlp *s, int M, int N, int K, const uint16_t *A, long sam, long sak, const uint16_t *B,
+tled_status gemm(tled_mlp *s, int M, int N, int K, const uint16_t *A, long lda, const uint16_t *B,
                  long sbk, long sbn, float *C, long scm, long scn, uint16_t *Act, const float *bias,
                  float *split_ext = nullptr, size_t split_ext_cap = 0) {
     const long tiles = long((M + BM - 1) / BM) * ((N + BN - 1) / BN);
@@ -1429,7 +1430,7 @@ tled_status gemm(tled_mlp *s, int M, int N, int K, const uint16_t *A, long sam, 
         nz = int(std::min<long>(64, std::max<long>(1, 512 / tiles)));
     int kchunk = ((K + nz - 1) / nz + BK - 1) / BK * BK;
     nz = (K + kchunk - 1) / kchunk;
-    const int am = load_mode(A, sam, sak), bmode = load_mode(B, sbn, sbk);
+    const int am = load_mode(A, lda, 1), bmode = load_mode(B, sbn, sbk);
     float *split = s->d_split;
     if (nz > 1 && split_ext) {
         const size_t need = size_t(nz) * M * N;
@@ -1461,12 +1462,10 @@ tled_status gemm(tled_mlp *s, int M, int N, int K, const uint16_t *A, long sam, 
     }
     float *Cout = nz > 1 ? split : C;
 #define TLED_GEMM_LAUNCH(AMODE, BMODE_)                                                                       \
-    hipLaunchKernelGGL((gemm_kernel<EPI, AMODE, BMODE_>), grid, dim3(kThreads), 0, s->stream, M, N, K, A, sam, sak, B, \
+    hipLaunchKernelGGL((gemm_kernel<EPI, AMODE, BMODE_>), grid, dim3(kThreads), 0, s->stream, M, N, K, A, lda, B, \
                        sbk, sbn, Cout, scm, scn, Act, bias, kchunk)
     if (am == LD_KVEC && bmode == LD_KVEC) TLED_GEMM_LAUNCH(LD_KVEC, LD_KVEC);
     else if (am == LD_KVEC && bmode == LD_RVEC) TLED_GEMM_LAUNCH(LD_KVEC, LD_RVEC);
-    else if (am == LD_RVEC && bmode == LD_RVEC) TLED_GEMM_LAUNCH(LD_RVEC, LD_RVEC);
-    else if (am == LD_RVEC && bmode == LD_KVEC) TLED_GEMM_LAUNCH(LD_RVEC, LD_KVEC);
     else TLED_GEMM_LAUNCH(LD_SCALAR, LD_SCALAR);
 #undef TLED_GEMM_LAUNCH
     if (nz > 1)
@@ -1611,13 +1610,13 @@ tled_status forward(tled_mlp *s, long n, const float *coords, const float *param
     int in = s->K0;
     for (int l = 0; l < s->cfg.depth; ++l) {
         const Layer &L = s->layers[l];
-        MTRY(gemm<EPI_BIAS_SILU>(s, int(n), W, in, a, in, 1, s->d_wb + L.w_off, 1, in, s->d_z[l], W, 1, s->d_a[l],
+        MTRY(gemm<EPI_BIAS_SILU>(s, int(n), W, in, a, in, s->d_wb + L.w_off, 1, in, s->d_z[l], W, 1, s->d_a[l],
                                  s->d_w + L.b_off));
         a = s->d_a[l];
         in = W;
     }
     const Layer &O = s->layers.back();
-    MTRY(gemm<EPI_BIAS_F32>(s, int(n), s->cfg.n_out, W, a, W, 1, s->d_wb + O.w_off, 1, W, s->d_y, s->cfg.n_out, 1,
+    MTRY(gemm<EPI_BIAS_F32>(s, int(n), s->cfg.n_out, W, a, W, s->d_wb + O.w_off, 1, W, s->d_y, s->cfg.n_out, 1,
                             nullptr, s->d_w + O.b_off));
     return TLED_OK;
 }
@@ -1711,10 +1710,10 @@ tled_status backward(tled_mlp *s, long n, const float *target, float *loss, cons
                            target, s->d_dy, s->d_part);
         MCHK(s, hipGetLastError());
         // dZ of a hidden layer: the next layer's times its weights, through the SiLU, in the GEMM's epilogue
-        MTRY(gemm<EPI_SILU_BACK>(s, int(n), W, no, s->d_dy, s->nop, 1, s->d_wb + O.w_off, W, 1, nullptr, W, 1,
+        MTRY(gemm<EPI_SILU_BACK>(s, int(n), W, no, s->d_dy, s->nop, s->d_wb + O.w_off, W, 1, nullptr, W, 1,
                                  s->d_dz[D - 1], s->d_z[D - 1]));
         for (int l = D - 1; l > 0; --l)
-            MTRY(gemm<EPI_SILU_BACK>(s, int(n), W, W, s->d_dz[l], W, 1, s->d_wb + s->layers[l].w_off, W, 1, nullptr, W, 1,
+            MTRY(gemm<EPI_SILU_BACK>(s, int(n), W, W, s->d_dz[l], W, s->d_wb + s->layers[l].w_off, W, 1, nullptr, W, 1,
                                      s->d_dz[l - 1], s->d_z[l - 1]));
     }
     MTRY(weight_gradients(s, n));
@@ -2001,7 +2000,7 @@ tled_status tled_mlp_gemm(tled_mlp *s, int32_t m, int32_t n, int32_t k, const ui
     if (!s || m <= 0 || n <= 0 || k <= 0 || !A || !B || !C) return TLED_E_ARG;
     MCHK(s, hipSetDevice(s->device));
     s->gemm_ms = s->fused_ms = s->gemm_flops = s->fused_flops = 0.0;
-    MTRY(gemm<EPI_F32>(s, m, n, k, A, k, 1, B, n, 1, C, n, 1, nullptr, nullptr));
+    MTRY(gemm<EPI_F32>(s, m, n, k, A, k, B, n, 1, C, n, 1, nullptr, nullptr));
     return TLED_OK;
 }
 
@@ -2010,7 +2009,7 @@ tled_status tled_mlp_gemm_static(tled_mlp *s, int32_t m, int32_t n, int32_t k, c
     if (!s || m <= 0 || n <= 0 || k <= 0 || !A || !B || !C) return TLED_E_ARG;
     if (!s->d_static_split) return mfail(s, TLED_E_STATE, "static scratch not resolved for this device");
     MCHK(s, hipSetDevice(s->device));
-    return gemm<EPI_F32>(s, m, n, k, A, k, 1, B, n, 1, C, n, 1, nullptr, nullptr, s->d_static_split,
+    return gemm<EPI_F32>(s, m, n, k, A, k, B, n, 1, C, n, 1, nullptr, nullptr, s->d_static_split,
                          kStaticSplitFloats);
 }
 
