@@ -101,7 +101,8 @@ typedef struct {
 /* Execution options (all optional; zero fields keep the defaults). */
 typedef struct {
     int32_t graph_steps;      /* steps per chunk: a chunk is one hipGraph replay (default 50;
-                                 < 0: eager launches in chunks of 100).  Monitors are reduced
+                                 < 0: eager launches in chunks of 100).  See also
+                                 tled_resident_counts.  Monitors are reduced
                                  at the last step of every chunk and of every tled_step call.
                                  Batches default to eager steps, each of which launches only
                                  the scenarios still running; a batch's graph launches those
@@ -133,15 +134,17 @@ typedef struct {
                                  100) serves the whole batch                                             */
     int32_t shared_update;    /* set before finalize.  How the nodes shared between patches are
                                  advanced (Eqs. 20 and 27 on their summed patch partials):
-                                 0: default (= 2); 1: inside the next step's patch kernel:
+                                 0: default: chunks of four or more steps of problems small
+                                 enough run in one kernel (tled_resident_counts), everything
+                                 else as 2; 1: inside the next step's patch kernel:
                                  every patch holding a shared node sums its partials and
                                  advances it while staging, the patch that wrote its first
                                  partial stores it, and one shared-node kernel ends each chunk
                                  (single problems with kernel_variant 2, 256-thread workgroups
                                  and neither the orthotropic expansion nor the tensor
                                  conduction; elsewhere as 2); 2: a shared-node kernel after
-                                 every step's patch kernel.  The fields are the same bits
-                                 either way                                                   */
+                                 every step's patch kernel, for every problem.  The fields are
+                                 the same bits either way                                     */
 } tled_options;
 
 typedef struct {
@@ -169,9 +172,11 @@ typedef struct {
     int64_t device_bytes;    /* device memory held by the handle                              */
     double  dt, dt_critical;
     int32_t patch_wgs_per_cu; /* fused variant on a device: resident patch workgroups per CU  */
-    int32_t shared_update;   /* fused variant with shared nodes: 1 advanced inside the next
-                                step's patch kernel, 2 by a kernel of their own each step (see
-                                tled_options.shared_update); else 0                           */
+    int32_t shared_update;   /* fused variant with shared nodes: what steps that are launched one
+                                by one do: 1 advanced inside the next step's patch kernel, 2 by
+                                a kernel of their own each step (see tled_options.shared_update;
+                                tled_resident_counts tells which chunks were not launched so);
+                                else 0                                                        */
     double  dt_thermal;      /* explicit thermal stability bound (Gershgorin, reference
                                 geometry, largest k and smallest c the material reaches);
                                 finalize refuses a dt above it                             */

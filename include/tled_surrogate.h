@@ -26,7 +26,11 @@
  * row-major): coords n x 3, params n x n_param, target n x n_out, out
  * n x n_out.  Calls run on the handle's stream; forward and train_step are
  * asynchronous except when a loss is requested.  Workspace grows on demand
- * to the largest n seen (hipMalloc), so the first call at a new size allocates.
+ * to the largest n seen (hipMalloc), so the first call at a new size allocates:
+ * fused inference needs none; gradients and training steps (and layer-by-layer
+ * inference) hold 2 K0 + 8 depth width + 4 n_out + 2 N bytes per sample, with K0
+ * the padded inputs and N the outputs padded to a multiple of 16, 10.6 kB for
+ * five layers of 256, and at most 64 copies of the gradient, usually 24.
  * Errors are tled_status codes (tled.h); messages via tled_mlp_last_error.
  */
 #ifndef TLED_SURROGATE_H
@@ -49,7 +53,7 @@ typedef struct {
     int32_t depth;     /* number of hidden layers (>= 1)                   */
     int32_t n_out;     /* outputs (<= 64)                                  */
     int32_t layerwise; /* 1: inference layer by layer through HBM; 0: fused
-                          (whole network per 64 samples in LDS) where the
+                          (whole network per 32 to 128 samples in LDS) where the
                           width is 64, 128 or 256 and depth <= 8            */
     float sigma;       /* standard deviation of the frequencies            */
     float init_scale;  /* uniform weight init bound factor (0: 1)          */
@@ -64,8 +68,8 @@ tled_status tled_mlp_set_stream(tled_mlp *mlp, void *hip_stream);
  * events between two streams, and after calls begun on other streams.  Another
  * thread's begin, get_params, set_params and set_stream wait for the end.  Every
  * begin that returned TLED_OK needs its end; a second begin, a set_stream in
- * between, or an end by a thread that has not begun returns TLED_E_STATE.  A handle is used either this way or
- * directly on its own stream.  Under stream capture the calls become part of the
+ * between, or an end by a thread that has not begun returns TLED_E_STATE.  A handle
+ * is used either this way or directly on its own stream.  Under stream capture the calls become part of the
  * graph; nothing orders its replays after calls on other streams. */
 tled_status tled_mlp_begin(tled_mlp *mlp, void *hip_stream);
 tled_status tled_mlp_end(tled_mlp *mlp);

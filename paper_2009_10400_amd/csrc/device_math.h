@@ -17,8 +17,12 @@
 // slots at 732 instructions per element when S was formed from C^-1 dev E by
 // matrix products and the conduction tensor from the total C): with N the stress
 // is two scalars times N and I, and for isotropic expansion the same N serves the
-// conduction, which leaves 549 (1M-tet ellipsoid: 28.5 -> 26.4 us per launch, 68 %
-// of the issue slots; the rest is memory and LDS latency).
+// conduction, which leaves 548 (1M-tet ellipsoid: 28.5 -> 26.4 us per launch, 69 %
+// of the issue slots; the rest is memory and LDS latency).  Taking the strain of an
+// isotropically heated element from the total gradient, with the thermal part
+// subtracted from the invariants, needs no fewer and loses accuracy: at a thermal
+// strain of 1e-2 and an elastic one of 1e-4 the stress error rose from 7.0e-6 to
+// 1.0e-5 of the stress, under a shrinkage of -0.05 from 3.5e-6 to 7.2e-6.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -166,8 +170,8 @@ __device__ __forceinline__ void add_axis_term(float He[9], const float H[9], con
 // (Dzz, Dxy, Dyz, Dxz)), read only inside the orthotropic expansion and tensor
 // conduction branches.  MODE (kIso, kTi, kOrtho) says which expansion and conduction
 // modes are compiled in: every mode a problem does not use costs registers in the
-// others' code (the H8 patch kernel takes 120 VGPRs with kIso and 127 with kTi, the
-// T4 one with two Prony terms 81 and 94; 64^3 H8 cube: 16.7 -> 14.9 us per launch
+// others' code (the H8 patch kernel takes 127 VGPRs with kIso and 126 with kTi, the
+// T4 one with two Prony terms 88 and 93; 64^3 H8 cube: 16.7 -> 14.9 us per launch
 // against all modes in one kernel that spilled).
 template <int NP, int MODE>
 __device__ __forceinline__ void element_physics(const KMat &m, const float H[9], const float gT[3],

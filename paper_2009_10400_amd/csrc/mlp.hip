@@ -838,13 +838,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void f
 // drift apart as they like: one's SiLU (half of the work) runs under another's products.
 // A tile's SiLU is done after the next tile's LDS reads have gone out.  The weights come
 // from a copy in the order of the matrix cores' fragments, 1 KB in a row per load: read
-// from the row-major matrix, every load touches 16 rows 512 bytes apart, and a layer
-// waited some 9500 cycles for its weights.  Measured, 5 layers of 256, 75 features: 1 M
-// samples 1.43 ms -> 0.80 ms (from the row-major weights 1.08; with one buffer, a barrier
-// per tile and two workgroups per CU 0.98), 1331 samples 33 -> 14 us.  What bounds it:
-// a layer's tile costs 1050 cycles where the products alone are 512 and the SiLU 490, so
-// the two overlap little; the features (6 % of the time), the output layer and the first
-// tile of each layer have no products to run under.
+// from the row-major matrix, every load touches 16 rows 512 bytes apart, and each layer
+// begins with a wait for its weights.  Measured, 5 layers of 256, 75 features: 1 M
+// samples 1.43 ms -> 0.78 to 0.82 ms (from the row-major weights 1.08; with one buffer, a
+// barrier per tile and two workgroups per CU 0.98), 1331 samples 33 -> 13 us.  What bounds
+// it: counted over the kernel, matrix cores are busy 33 % of the time, vector instructions
+// issue in 54 % and LDS works in 43 %, half of it bank conflicts, so the three overlap
+// little; the features, the output layer and the first tile of each layer have no products
+// to run under.
 // Products, their order and the epilogue arithmetic are those of the layer-by-layer
 // GEMMs, so the outputs have the same bits.
 constexpr int kTiledK = 8;            // 32-deep k steps of a layer held in registers: inputs up to 256

@@ -3,7 +3,7 @@
 //
 // A small or medium problem spends its step on the two launches of the patch and
 // shared-node kernels and on staging state that has not left the chip's reach: the
-// 6000-tet cube took 7.8 us per step for 0.1 us of arithmetic and traffic.  Here
+// 6000-tet cube takes 7.9 us per step for 0.1 us of arithmetic and traffic.  Here
 // every patch has a workgroup of its own that keeps its nodes in LDS and its Prony
 // state in registers for k steps, and exchanges the partial sums of the nodes it
 // shares with other patches through memory, every step.
@@ -36,10 +36,11 @@
 // that runs, and that itself waits only for partials of earlier steps or of the same
 // step written before its own wait; a bound on the polls stays as a guard.
 //
-// What is left per step (6000-tet cube, 3.9 us; 83k-tet ellipsoid, 6.2 against 9.0 with
-// the per-step launches; 27^3 H8, 6.5 against 9.6): one element's dependent arithmetic
-// (1.1 us), two passes over LDS slots (0.5 us) and one trip of a partial from store to
-// load past the L2 caches (1.8 us, more with more workgroups).
+// What is left per step (in chunks of 50, against the per-step launches: 6000-tet cube
+// 4.2 and 7.9 us, 83k-tet ellipsoid 6.5 and 9.1, 27^3 H8 6.4 and 9.7) is a chain: one
+// element's dependent arithmetic, two passes over LDS slots and one trip of a partial from
+// store to load past the L2 caches, which is longer with more workgroups.  No unit is busy:
+// vector instructions issue in 16 % of the cube's cycles and 28 % of the ellipsoid's.
 //
 // Bits.  The element, node and summation code is that of the patch kernels, in the
 // same order, so a chunk gives the same bits either way.

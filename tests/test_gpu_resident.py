@@ -106,8 +106,9 @@ def test_two_problems_in_turn_on_their_own_streams():
 
 
 def test_rewound_state_does_not_meet_old_partials():
-    """The exchanged words carry the step they belong to; going back to an earlier state must not
-    find words of the first pass over the same steps."""
+    """A slot of the exchange is empty until its partial of the step is written, and a chunk empties all
+    slots before its first step; going back to an earlier state must not find partials of the first
+    pass over the same steps."""
     from paper_2009_10400_amd import tled
     p = problem("t4_cube")
     s = tled.from_problem(p, device=0)
