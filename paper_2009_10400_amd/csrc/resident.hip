@@ -20,7 +20,7 @@
 // stores, behind the element work) before this patch publishes step j, which they
 // read first.  The first chunk step finds all slots empty: every workgroup empties its
 // own before the meeting below.  (With four 8-byte words (value, step) per partial, the
-// 83k-tet ellipsoid took 33 us per step, bound by the requests; 6.2 us like this.)
+// 83k-tet ellipsoid took 33 us per step, bound by the requests; 6.6 us like this.)
 //
 // Waiting.  A workgroup waits for others, so all must be resident.  Before the first
 // step they meet: the last to arrive decides GO; one that has waited meet_ticks decides
@@ -37,7 +37,7 @@
 // step written before its own wait; a bound on the polls stays as a guard.
 //
 // What is left per step (in chunks of 50, against the per-step launches: 6000-tet cube
-// 4.2 and 7.9 us, 83k-tet ellipsoid 6.5 and 9.1, 27^3 H8 6.4 and 9.7) is a chain: one
+// 4.4 and 7.9 us, 83k-tet ellipsoid 6.6 and 9.2, 27^3 H8 6.5 and 9.5) is a chain: one
 // element's dependent arithmetic, two passes over LDS slots and one trip of a partial from
 // store to load past the L2 caches, which is longer with more workgroups.  No unit is busy:
 // vector instructions issue in 16 % of the cube's cycles and 28 % of the ellipsoid's.
