@@ -821,7 +821,8 @@ def main():
                    "shared_node_fraction": info["n_shared_nodes"] / max(1, info["n_nodes"]),
                    "patch_lds_bytes": info["patch_lds_bytes"],
                    "patch_wgs_per_cu": info["patch_wgs_per_cu"],
-                   "shared_update": {1: "fused into the next step's patch kernel",
+                   "shared_update": "inside chunks of steps in one kernel" if sim.resident_counts()["chunks"] else
+                                    {1: "fused into the next step's patch kernel",
                                      2: "shared-node kernel every step"}.get(info["shared_update"], "none"),
                    "patch_order": {-1: "as generated", 2: "Morton runs"}.get(args.reorder, "coordinate bisection"),
                    "dt": sim.dt},
